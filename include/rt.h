@@ -70,7 +70,8 @@ enum { RT_QUAD_GAUSS_LEGENDRE = 0, RT_QUAD_LEVEL_SYMMETRIC = 1 };
  * after every step the gas momentum change of the step moves the flow,
  * v <- v + d(rho v)/rho, in rt_fields.v, and the next step's interface flow
  * speeds and IV follow (Section 5.2, equilibrium in a moving medium).  Angle
- * sets of at most 320 directions; not for served requests. */
+ * sets of at most 320 directions and planes (the intensities of one direction)
+ * of at most 4 GiB, else RT_EUNSUPPORTED; not for served requests. */
 #define RT_GAS_FEEDBACK 2u
 /* Flag: the original transport that Section 4.2 starts from (Stone &
  * Mihalas 1992): every interface at speed C (alpha = 1) and I itself

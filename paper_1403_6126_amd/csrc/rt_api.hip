@@ -458,6 +458,9 @@ int ctx_init_host(const rt_grid *g, const rt_angles *an, const rt_params *p, rt_
   if (!(p->c_reduced >= 0.0) || p->c_reduced > p->c) return RT_EINVAL;
   if (p->c_reduced > 0.0 && p->c_reduced < p->c && (p->flags & RT_ESTIMATE_V))
     return RT_EUNSUPPORTED;
+  const bool tiles = plane_fits(nc, p->precision == RT_FP32_MIXED ? 4 : 8);
+  // the thread-per-cell kernels hold the velocity fixed
+  if (!tiles && (p->flags & RT_GAS_FEEDBACK)) return RT_EUNSUPPORTED;
 
   c->g = *g;
   c->p = *p;
@@ -491,9 +494,9 @@ int ctx_init_host(const rt_grid *g, const rt_angles *an, const rt_params *p, rt_
   // second order: the fused step runs both absorption solves on the
   // wave-group kernel; the step from a given dF on the thread-per-cell one
   c->shape.second = (p->flags & RT_SECOND_ORDER) != 0;
-  if (p->precision == RT_FP32_MIXED)
+  if (tiles && p->precision == RT_FP32_MIXED)
     pick_shape32(N, c->shape);
-  else
+  else if (tiles)
     pick_shape64(N, *g, nc, c->shape);
   c->nblocks = (nc + 63) / 64;  // enough partial-total rows for either kernel
   // angle records: every slot of the wave-group kernel has one (padding

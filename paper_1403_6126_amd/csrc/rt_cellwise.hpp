@@ -4,8 +4,8 @@
 // the per-cell sums of the reduced absorption / scattering systems and
 // stages p_m in the output buffer; pass 2 forms I^{n+1}.  Used for what the
 // wave kernels do not take: FP32 sets of more than 320 directions, the FP64
-// second-order step beyond 360 directions or from a given increment, the FP32
-// transport-only entry point, and the moments.
+// second-order step beyond 360 directions or from a given increment, planes of
+// more than 4 GiB, the FP32 transport-only entry point, and the moments.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -22,6 +22,13 @@ constexpr int kAnglesPerWave = 10;
 constexpr int kMaxGroupsPerWave = 4;
 constexpr int kMaxFeedbackAngles = 320;
 
+// The wave-group kernels address a plane (the intensities of one angle) by
+// 32-bit byte offsets; larger planes, more than 2^29 cells in FP64 and 2^30 in
+// FP32, run on the thread-per-cell kernels, which index by 64 bits.
+constexpr bool plane_fits(long long ncell, int storage_bytes) {
+  return ncell * storage_bytes <= (1ll << 32);
+}
+
 // Geometry of the FP64 kernel, passed to it by value.
 struct Geo64 {
   int slots = 0, chunks = 1;  // angles per wave and chunk; chunks of waves*slots angles

@@ -1,6 +1,7 @@
 // Step launches with FP32 intensities: the wave-group kernels by number of
 // angle groups per wave, and the thread-per-cell kernel for more directions
-// than they hold and for second-order steps from a given increment.
+// than they hold, for second-order steps from a given increment and for planes
+// of more than 4 GiB.
 #include "rt_cellwise.hpp"
 #include "rt_internal.hpp"
 

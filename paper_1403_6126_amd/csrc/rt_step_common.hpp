@@ -59,7 +59,7 @@ __device__ __forceinline__ float vl_half_product(float a, float b) {
 
 // Element idx of an angle plane, addressed by a 32-bit byte offset from the
 // wave-uniform start of the plane (one scalar base and one vector register
-// per load).  rt_create keeps every plane below 4 GiB.
+// per load): planes of up to 4 GiB (plane_fits).
 template <typename S>
 __device__ __forceinline__ S plane_ld(const S *plane, unsigned idx) {
   const unsigned off = idx * (unsigned)sizeof(S);
@@ -68,11 +68,12 @@ __device__ __forceinline__ S plane_ld(const S *plane, unsigned idx) {
 
 // The same read as a raw buffer load: the plane is a buffer resource held in
 // scalar registers, the lane's byte offset one vector register, so no vector
-// address arithmetic is needed (gfx9 resource word 3 for raw loads).
+// address arithmetic is needed (gfx9 resource word 3 for raw loads).  The
+// resource spans the whole 32-bit range: a read past its end returns zero.
 template <typename S>
 __device__ __forceinline__ S plane_buf_ld(const S *plane, unsigned idx) {
   const __amdgpu_buffer_rsrc_t r =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(plane), 0, 0x7fffffff, 0x00020000);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<S *>(plane), 0, -1, 0x00020000);
   const unsigned off = idx * (unsigned)sizeof(S);
   if constexpr (sizeof(S) == 8)
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
