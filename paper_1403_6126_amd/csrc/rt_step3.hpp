@@ -409,17 +409,17 @@ __device__ __forceinline__ void step3_tile(const StepArgs &p, int blk, int g, in
           if (pos) {
             const A Im2 = plane_value<S, A, PER>(p, r[2], s.idx[0], s.kind[0], 0, d, mc, pos, ghosts);
             const A D0 = (Im1 - Im2) - V[0] * invC;
-            const A qm = vl_half_product(D0, D1), q0 = vl_half_product(D1, D2);
+            const A qm = vl_half(D0, D1), q0 = vl_half(D1, D2);
             T = s.cbR * D2 + (s.caL + s.cbL) * D1 + h2 * (s.caR * q0 - s.caL * qm);
           } else {
             const A Ip2 = plane_value<S, A, PER>(p, r[2], s.idx[3], s.kind[3], 1, d, mc, pos, ghosts);
             const A D3 = (Ip2 - Ip1) - V[3] * invC;
-            const A q0 = vl_half_product(D1, D2), qp = vl_half_product(D2, D3);
+            const A q0 = vl_half(D1, D2), qp = vl_half(D2, D3);
             T = (s.caR + s.cbR) * D2 + s.cbL * D1 - h2 * (s.caR * qp - s.caL * q0);
           }
           // IV faces: the upwind cell of each face by the sign of its flow
-          const A qvL = vl_half_product(s.fL > A(0) ? V[0] : V[2], V[1]);
-          const A qvR = vl_half_product(s.fR > A(0) ? V[1] : V[3], V[2]);
+          const A qvL = vl_half(s.fL > A(0) ? V[0] : V[2], V[1]);
+          const A qvR = vl_half(s.fR > A(0) ? V[1] : V[3], V[2]);
           T += s.rR * V[2] + s.lL * V[1] + (s.fR * qvR - s.fL * qvL);
           dF[k] -= mud * T;
         }

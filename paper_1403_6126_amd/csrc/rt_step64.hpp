@@ -44,8 +44,11 @@ enum Mode64 : int { kFused64 = 0, kSource64 = 1 };
 // with Ca = C alpha, Cb = C (1 - alpha)/2, h2 = 1 - nu, r the upper cell's
 // share of the IV value and f its signed slope factor (all times dt/dx).
 // Relative to the upper cell it is G - C dt/dx (I_+1 - I_0), since the value
-// of I~ and that of IV add to I.  The increment of a cell is -mu times the
-// difference of its two faces relative to the cell.
+// of I~ and that of IV add to I; as Ca + 2 Cb = C this is the same sum with
+// k - C = -Cb - Ca (mu > 0), -Cb (mu < 0) in place of k and r - 1 = -l in place
+// of r, which is how it is formed: a face beside an empty upwind cell is then
+// zero exactly, relative to that cell.  The increment of a cell is -mu times
+// the difference of its two faces relative to the cell.
 struct Face64 {
   unsigned idx[4];  // cells at offsets -1, 0, +1, +2 (wrapped, or the edge cell)
   unsigned kinds;   // bit j: cell j is a ghost of a fixed or vacuum face
@@ -54,6 +57,7 @@ struct Face64 {
   double wp[3];     // W(+2) - W(+1): the interval above
   double wf[3];     // wm or wp, the one upwind by the flow of the face
   double ca, cb, r, f;
+  double l;         // dt/dx - r, the lower cell's share
 };
 constexpr int kFaceVals = 16, kFaceWords = 5;
 
@@ -131,6 +135,7 @@ __device__ __forceinline__ void load_face64(const StepArgs &p, int cb, int k, in
     for (int t = 0; t < 3; ++t) W[j][t] = p.mom_in[(size_t)(10 + t) * N + cell[j]];
   }
   face_coef64<PER>(p, cell[1], cell[2], k, d, f.ca, f.cb, f.r, f.f);
+  f.l = p.dt_dx[d] - f.r;
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     f.wm[t] = W[1][t] - W[0][t];
@@ -160,7 +165,7 @@ __device__ __forceinline__ void face_put(char *b, const Face64 &f, int lane) {
   for (int j = 0; j < 4; ++j) w[j * 64] = f.idx[j];
   w[4 * 64] = f.kinds;
 }
-__device__ __forceinline__ void face_get(const char *b, Face64 &f, int lane) {
+__device__ __forceinline__ void face_get(const char *b, double dt_dx, Face64 &f, int lane) {
   const double *v = reinterpret_cast<const double *>(b) + lane;
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
@@ -172,6 +177,7 @@ __device__ __forceinline__ void face_get(const char *b, Face64 &f, int lane) {
   f.ca = v[12 * 64];
   f.cb = v[13 * 64];
   f.r = v[14 * 64];
+  f.l = dt_dx - f.r;
   f.f = v[15 * 64];
   const unsigned *w = reinterpret_cast<const unsigned *>(b + 64 * kFaceVals * 8) + lane;
 #pragma unroll
@@ -293,24 +299,27 @@ __device__ __forceinline__ void ghost_reads(const StepArgs &p, const unsigned (&
 // lower cell and Gp relative to the upper one.
 __device__ __forceinline__ void face_value(const Face64 &f, double n0, double n1, double n2,
                                            double hs, bool pos, double I0, double I1, double If,
-                                           double invC, double cdt, double &G, double &Gp) {
+                                           double invC, double &G, double &Gp) {
   const double V = n0 * f.w0[0] + n1 * f.w0[1] + n2 * f.w0[2];
   const double Vf = n0 * f.wf[0] + n1 * f.wf[1] + n2 * f.wf[2];
-  double Vx, dx, k;
+  const double cab = f.ca + f.cb;
+  double Vx, dx, k, kp;
   if (pos) {
     Vx = n0 * f.wm[0] + n1 * f.wm[1] + n2 * f.wm[2];
     dx = I0 - If;
     k = f.cb;
+    kp = cab;
   } else {
     Vx = n0 * f.wp[0] + n1 * f.wp[1] + n2 * f.wp[2];
     dx = If - I1;
-    k = f.ca + f.cb;
+    k = cab;
+    kp = f.cb;
   }
-  const double dI = I1 - I0;
-  const double D = fma_(-V, invC, dI), Dx = fma_(-Vx, invC, dx);
+  const double D = fma_(-V, invC, I1 - I0), Dx = fma_(-Vx, invC, dx);
   const double q = vl_half(Dx, D), qv = vl_half(Vf, V);
-  G = fma_(hs * f.ca, q, k * D) + fma_(f.r, V, f.f * qv);
-  Gp = fma_(-cdt, dI, G);
+  const double slopes = fma_(hs * f.ca, q, f.f * qv);
+  G = fma_(k, D, fma_(f.r, V, slopes));
+  Gp = fma_(-kp, D, fma_(-f.l, V, slopes));
 }
 
 // One lane up: lane l receives lane l - 1's value (lane 0 receives 0).
@@ -396,16 +405,11 @@ struct Transport64 {
                (cptr<double>)(p.arec + (long long)m * kRec), (long long)p.ncell, NA - 1 - m0};
   }
 
-  __device__ static __forceinline__ double half_slope(double a, double b) {
-    return NS <= 4 ? vl_half_product(a, b) : vl_half(a, b);
-  }
-
   // One shared axis: every lane forms its high face; below(k, Gp) gives the
   // face below relative to the cell and may keep Gp.
   template <typename Below>
   __device__ __forceinline__ void shared_axis(const Face64 &f, int d,
                                               double (&dF)[NS], Below below) const {
-    const double cdt = p.C * p.dt_dx[d];
     const Set set = open();
     // some lane of the wave has a ghost cell along this axis (wave-uniform)
     const bool gh = !PER && __any(f.kinds != 0);
@@ -435,7 +439,7 @@ struct Transport64 {
       const double mud = R.mud;
       if (!PER && gh) ghost_reads(p, f.idx, f.kinds, d, m0 + k, pos, r[0], r[1], r[2]);
       double G, Gp;
-      face_value(f, R.n0, R.n1, R.n2, R.h, pos, r[0], r[1], r[2], invC, cdt, G, Gp);
+      face_value(f, R.n0, R.n1, R.n2, R.h, pos, r[0], r[1], r[2], invC, G, Gp);
       const double lo = below(k, Gp);
       dF[k] = fma_(-mud, G - lo, dF[k]);
     }
@@ -476,19 +480,19 @@ struct Transport64 {
       for (int j = 0; j < 4; ++j) V[j] = n0 * s.w[j][0] + n1 * s.w[j][1] + n2 * s.w[j][2];
       const double D1 = fma_(-V[1], invC, r[3] - r[0]);
       const double D2 = fma_(-V[2], invC, r[1] - r[3]);
-      const double q0 = half_slope(D1, D2);
+      const double q0 = vl_half(D1, D2);
       double T;
       if (pos) {
         const double D0 = fma_(-V[0], invC, r[0] - r[2]);
-        const double qm = half_slope(D0, D1);
+        const double qm = vl_half(D0, D1);
         T = s.cbR * D2 + (s.caL + s.cbL) * D1 + h2 * (s.caR * q0 - s.caL * qm);
       } else {
         const double D3 = fma_(-V[3], invC, r[2] - r[1]);
-        const double qp = half_slope(D2, D3);
+        const double qp = vl_half(D2, D3);
         T = (s.caR + s.cbR) * D2 + s.cbL * D1 - h2 * (s.caR * qp - s.caL * q0);
       }
-      const double qvL = half_slope(s.fL > 0.0 ? V[0] : V[2], V[1]);
-      const double qvR = half_slope(s.fR > 0.0 ? V[1] : V[3], V[2]);
+      const double qvL = vl_half(s.fL > 0.0 ? V[0] : V[2], V[1]);
+      const double qvR = vl_half(s.fR > 0.0 ? V[1] : V[3], V[2]);
       T += s.rR * V[2] + s.lL * V[1] + (s.fR * qvR - s.fL * qvL);
       dF[k] -= mud * T;
     }
@@ -502,7 +506,7 @@ template <int NS, bool PER>
 __device__ __forceinline__ void start_faces(const StepArgs &p, int cfirst, int climit, int x0,
                                             int nst, int m0, int lane, double *tab) {
   const int nx = p.n[0];
-  const double invC = p.invC, cdt = p.C * p.dt_dx[0];
+  const double invC = p.invC;
   const unsigned inv = 65536u / (unsigned)nst + 1u;
   for (int b = 0; b < NS * nst; b += 64) {
     const int pr = b + lane;
@@ -522,7 +526,7 @@ __device__ __forceinline__ void start_faces(const StepArgs &p, int cfirst, int c
     double r0 = I[f.idx[1]], r1 = I[f.idx[2]], rf = I[pos ? f.idx[0] : f.idx[3]];
     if (!PER && __any(f.kinds != 0)) ghost_reads(p, f.idx, f.kinds, 0, m, pos, r0, r1, rf);
     double G, Gp;
-    face_value(f, mud, R[rec_n1], R[rec_n2], R[rec_s0], pos, r0, r1, rf, invC, cdt, G, Gp);
+    face_value(f, mud, R[rec_n1], R[rec_n2], R[rec_s0], pos, r0, r1, rf, invC, G, Gp);
     if (on) tab[k * kMaxStarts + j] = Gp;
   }
 }
@@ -626,7 +630,7 @@ struct Tile64 {
     const Transport tr{p, lane, m0, p.nang, (unsigned)c, p.invC};
     if (xs) {
       Face64 f;
-      face_get(lds + L.face_x, f, lane);
+      face_get(lds + L.face_x, p.dt_dx[0], f, lane);
       const double *tab = table() + mystart;
       tr.shared_axis(f, 0, dF, [&](int k, double Gp) {
         const double s = tab[k * kMaxStarts], b = lane_below(Gp);

@@ -17,32 +17,16 @@ constexpr int kRows = 13;        // folded sums, the values of the largest round
 __device__ __forceinline__ double fma_(double a, double b, double c) {
   return __builtin_fma(a, b, c);
 }
-// x limited to [0, 1], a NaN to 0 (the clamp modifier of the instruction
-// that makes x)
-__device__ __forceinline__ double clamp01(double x) { return fmin(fmax(x, 0.0), 1.0); }
-
 // Half the van Leer harmonic-mean slope of two consecutive differences:
 // ab/(a + b) when ab > 0, else 0 (zero at extrema).  The upwind interface
 // value of the monotonic piecewise-linear reconstruction at Courant number
 // nu is the upwind cell's value plus (1 - nu) times this, signed by the
-// direction.  Written with phi = b/(a + b) as (a + b) (phi - phi^2): the
-// parabola is positive (at most 1/4) exactly where a and b have the same
-// sign, so the test for extrema is the clamp to [0, 1] of one multiply-add,
-// which also takes the 0/0 of a = b = 0 to zero (a NaN in a or b stays one
-// through the sum).  Seven instructions in FP64, the reciprocal among them,
-// where the product, the quotient, a compare and two selects take nine.
+// direction.  It is symmetric in a and b, odd under a, b -> -a, -b, exactly
+// zero beside a zero difference (an empty cell has nothing to send out), and its
+// rounding is relative to the slope.  The parabola (a + b) (phi - phi^2) of
+// phi = b/(a + b), two instructions shorter, has none of this: its error is
+// relative to the larger difference.
 __device__ __forceinline__ double vl_half(double a, double b) {
-  const double s = a + b;
-  const double phi = b * limiter_rcp(s);
-  return s * clamp01(fma_(-phi, phi, phi));
-}
-// The product form.  FP32 keeps it: the two forms round differently, by the
-// same amount, and one unit of rounding in FP32 intensities is 1e-5 of the
-// momentum change of a step, which is a small difference of their moments.
-// FP64 keeps it for sets of up to four directions, which run on one wave and
-// are not bound by the limiter: without opacity the gas changes are the
-// rounding of two equal sums, and stay what they were bit for bit.
-__device__ __forceinline__ double vl_half_product(double a, double b) {
   const double ab = a * b;
   const double q = ab * limiter_rcp(a + b);
   return ab > 0.0 ? q : 0.0;
@@ -53,7 +37,7 @@ extern "C" __device__ __attribute__((const)) float fmul_legacy(float, float) __a
     "llvm.amdgcn.fmul.legacy");
 // In FP32 the same value without the compare: max(ab, 0) times the reciprocal by
 // the multiplication whose product with zero is zero (also where a + b = 0).
-__device__ __forceinline__ float vl_half_product(float a, float b) {
+__device__ __forceinline__ float vl_half(float a, float b) {
   return fmul_legacy(fmaxf(a * b, 0.0f), limiter_rcp(a + b));
 }
 
