@@ -52,8 +52,9 @@ namespace rtk {
 // face's upwind cell.
 template <typename A>
 struct AxisData {
-  unsigned idx[4];  // cells at offsets -2, -1, +1, +2 (wrapped, or the edge cell)
-  int kind[4];      // 1: a ghost of a fixed or vacuum face
+  unsigned idx[4];  // cells at offsets -2, -1, +1, +2 (wrapped, the edge cell, or the
+                    // place in the face of a fixed ghost)
+  int kind[4];      // 0 read the cell, 1 fixed table, 2 vacuum
   A dW[4][3];       // W(-1)-W(-2), W(0)-W(-1), W(+1)-W(0), W(+2)-W(+1)
   A caL, cbL, caR, cbR;
   A lL, rR;         // l of the low face, 1 - l of the high face
@@ -80,11 +81,15 @@ __device__ __forceinline__ void load_axis(const StepArgs &p, int c, const int q[
         kk -= kk >= n ? n : 0;
       } else {
         kk = k < 0 ? 0 : n - 1;
-        kind = bc == kFixed || bc == kVacuum ? 1 : 0;
+        kind = bc == kFixed ? 1 : bc == kVacuum ? 2 : 0;
       }
     }
     const int cj = c + (kk - q[d]) * p.stride[d];
-    s.idx[j] = (unsigned)cj;
+    // a ghost of a fixed face: its place in a position-dependent table
+    s.idx[j] = PER || kind != 1 ? (unsigned)cj
+               : d == 0         ? (unsigned)(q[1] + p.n[1] * q[2])
+               : d == 1         ? (unsigned)(q[0] + p.n[0] * q[2])
+                                : (unsigned)(q[0] + p.n[0] * q[1]);
     s.kind[j] = kind;
 #pragma unroll
     for (int t = 0; t < 3; ++t) W[j][t] = A(p.mom_in[(size_t)(10 + t) * N + cj]);
@@ -101,7 +106,7 @@ __device__ __forceinline__ void load_axis(const StepArgs &p, int c, const int q[
   s.lL = A(p.faces[(size_t)(d * 3 + 1) * N + c]);
   s.fL = A(p.faces[(size_t)(d * 3 + 2) * N + c]);
   if (PER || q[d] + 1 < n || p.bc[d][1] == kPeriodic) {
-    const unsigned cr = s.idx[2];
+    const unsigned cr = s.idx[2];  // a cell here, no ghost
     s.caR = A(p.faces[(size_t)(d * 3 + 0) * N + cr]);
     s.rR = A(1.0 - p.faces[(size_t)(d * 3 + 1) * N + cr]);
     s.fR = A(p.faces[(size_t)(d * 3 + 2) * N + cr]);
@@ -127,17 +132,42 @@ __device__ __forceinline__ void load_axis(const StepArgs &p, int c, const int q[
   s.fR *= dtdx;
 }
 
-// Intensity at a stencil cell from the value raw read at its (clamped) cell
-// idx of the angle plane, with the ghost kinds.  ghosts (wave-uniform): some
-// lane of the wave has a ghost cell along this axis; without any, the
-// per-lane kind tests are skipped by a scalar branch.
-template <typename S, typename A, bool PER>
-__device__ __forceinline__ A plane_value(const StepArgs &p, S raw, int idx, int kind, int side,
-                                         int d, int m, bool pos, bool ghosts) {
-  if (PER || !ghosts) return A(raw);
-  double gv;
-  if (!ghost_value(p, idx, kind != 0, side, d, m, side == 0 ? pos : !pos, gv)) return A(raw);
-  return kind ? A(gv) : A(raw);
+// The ghost cells of a wave along one axis.  flags (wave-uniform): bit j, some
+// lane's stencil cell j is a ghost of a fixed or vacuum face; bit 4 + side, the
+// face is a vacuum; bit 6 + side, it has a position-dependent table.  table[side]:
+// lane k holds the ghost intensity of the wave's slot k there (the angle table's, or
+// zero), so that a slot takes it by a lane read.
+// Nearly every wave of a grid with rows of up to a hundred cells has a ghost, so
+// what a slot does about them decides the time of such grids: no load of the
+// face's kind or table, no integer division for the place in a table, and one
+// branch past all of it.  (47 x 51 x 81, 168 directions, y faces vacuum and copy,
+// 18 steps: 8.1 ms; 8.9 with per-lane tests at each read, 11.2 with scalar loads
+// at each read.  256^3 S8 between fixed faces: 13.3, 15.7 and 15.6 ms.)
+template <typename A>
+struct AxisGhosts {
+  unsigned flags;
+  A table[2];
+};
+
+// The ghost intensity of slot k (angle m) beyond the low or high face: the fixed
+// table's (read only where the outermost cell of the stencil is a ghost, with its
+// place idx in a position-dependent table), or zero for the incoming directions of a
+// vacuum face; false where the ghost copies the edge cell.  Both ghost layers have
+// the value of the face cell.  The tests are on scalars.
+template <typename A>
+__device__ __forceinline__ bool ghost_of(const StepArgs &p, const AxisGhosts<A> &G, int idx,
+                                         int ghost, int side, int d, int k, int m, bool incoming,
+                                         A &v) {
+  v = A(0);
+  if ((G.flags >> (4 + side)) & 1u) return incoming;
+  if ((G.flags >> (6 + side)) & 1u) {
+    const int nf = d == 0 ? p.n[1] * p.n[2] : d == 1 ? p.n[0] * p.n[2] : p.n[0] * p.n[1];
+    if (ghost) v = A(p.gface[d * 2 + side][(size_t)m * (size_t)nf + idx]);
+  } else {
+    v = __builtin_bit_cast(
+        A, __builtin_amdgcn_readlane(__builtin_bit_cast(int, G.table[side]), k));
+  }
+  return true;
 }
 
 // The temperature and scattering solve on every wave (1) or on wave 0 with
@@ -340,9 +370,21 @@ __device__ __forceinline__ void step3_tile(const StepArgs &p, int blk, int g, in
       if (CELL_EARLY && d == p.ndim - 1) cell_load();
       AxisData<A> s;
       axis_get<A, PER>(lds, d, s, lane);
-      // does any lane of the wave have a ghost cell along this axis
-      const bool ghosts =
-          !PER && __any(s.kind[0] | s.kind[1] | s.kind[2] | s.kind[3]) != 0;
+      AxisGhosts<A> gh{};
+      if constexpr (!PER) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) gh.flags |= __any(s.kind[j]) ? 1u << j : 0u;
+        if (gh.flags) {
+          const int ml = m0 + slot_off(lane), mg = ml < NA ? ml : NA - 1;
+#pragma unroll
+          for (int side = 0; side < 2; ++side) {
+            const bool fixed = p.bc[d][side] == kFixed, face = p.gface[d * 2 + side] != nullptr;
+            if (p.bc[d][side] == kVacuum) gh.flags |= 16u << side;
+            if (fixed && face) gh.flags |= 64u << side;
+            if (fixed && !face) gh.table[side] = A(p.ghost[(size_t)(d * 2 + side) * NA + mg]);
+          }
+        }
+      }
       // the plane reads of a slot: cells -1 and +1 and the far upwind cell
       // (-2 for mu_d > 0, else +2).  Those of the PF next slots of the axis
       // are issued before the arithmetic of the current one, so that their
@@ -400,22 +442,43 @@ __device__ __forceinline__ void step3_tile(const StepArgs &p, int blk, int g, in
 #pragma unroll
           for (int j = 0; j < 4; ++j) V[j] = n0 * s.dW[j][0] + n1 * s.dW[j][1] + n2 * s.dW[j][2];
           const bool pos = (fl >> d) & 1u;
-          const A Im1 = plane_value<S, A, PER>(p, r[0], s.idx[1], s.kind[1], 0, d, mc, pos, ghosts);
-          const A Ip1 = plane_value<S, A, PER>(p, r[1], s.idx[2], s.kind[2], 1, d, mc, pos, ghosts);
+          if (!PER && gh.flags) {
+            if (gh.flags & 3u) {
+              A v;
+              if (ghost_of<A>(p, gh, s.idx[0], s.kind[0], 0, d, k, mc, pos, v)) {
+                r[0] = s.kind[1] ? v : r[0];
+                if (pos) r[2] = s.kind[0] ? v : r[2];
+              }
+            }
+            if (gh.flags & 12u) {
+              A v;
+              if (ghost_of<A>(p, gh, s.idx[3], s.kind[3], 1, d, k, mc, !pos, v)) {
+                r[1] = s.kind[2] ? v : r[1];
+                if (!pos) r[2] = s.kind[3] ? v : r[2];
+              }
+            }
+          }
+          const A Im1 = A(r[0]);
+          const A Ip1 = A(r[1]);
           const A ick = IC_REG ? Ic[IC_REG ? k : 0] : A(r[3]);
           const A D1 = (ick - Im1) - V[1] * invC;
           const A D2 = (Ip1 - ick) - V[2] * invC;
+          // c2 D2 + c1 D1, the product that is rounded by itself named where the
+          // compiler's choice would follow from the ghost tests around it
+          auto pair = [&](A c2, A c1) {
+            return PER ? c2 * D2 + c1 * D1 : __builtin_fmaf(c1, D1, c2 * D2);
+          };
           A T;
           if (pos) {
-            const A Im2 = plane_value<S, A, PER>(p, r[2], s.idx[0], s.kind[0], 0, d, mc, pos, ghosts);
+            const A Im2 = A(r[2]);
             const A D0 = (Im1 - Im2) - V[0] * invC;
             const A qm = vl_half(D0, D1), q0 = vl_half(D1, D2);
-            T = s.cbR * D2 + (s.caL + s.cbL) * D1 + h2 * (s.caR * q0 - s.caL * qm);
+            T = pair(s.cbR, s.caL + s.cbL) + h2 * (s.caR * q0 - s.caL * qm);
           } else {
-            const A Ip2 = plane_value<S, A, PER>(p, r[2], s.idx[3], s.kind[3], 1, d, mc, pos, ghosts);
+            const A Ip2 = A(r[2]);
             const A D3 = (Ip2 - Ip1) - V[3] * invC;
             const A q0 = vl_half(D1, D2), qp = vl_half(D2, D3);
-            T = (s.caR + s.cbR) * D2 + s.cbL * D1 - h2 * (s.caR * qp - s.caL * q0);
+            T = pair(s.caR + s.cbR, s.cbL) - h2 * (s.caR * qp - s.caL * q0);
           }
           // IV faces: the upwind cell of each face by the sign of its flow
           const A qvL = vl_half(s.fL > A(0) ? V[0] : V[2], V[1]);

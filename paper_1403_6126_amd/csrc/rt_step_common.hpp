@@ -113,24 +113,6 @@ __device__ __forceinline__ void stream_store(T *p, T v) {
     *p = v;
 }
 
-// The ghost intensity of angle m beside edge cell e beyond the fixed or vacuum
-// face (d, side), read only where `here`; incoming: the direction enters through
-// the face.  False where the ghost copies the edge cell (outgoing directions of a
-// vacuum face).  The kind of face is the same for the whole grid, so the tests
-// are scalar.
-__device__ __forceinline__ bool ghost_value(const StepArgs &p, int e, bool here, int side, int d,
-                                            int m, bool incoming, double &v) {
-  const int bc = p.bc[d][side];
-  v = 0.0;
-  if (bc != kFixed) return bc == kVacuum && incoming;
-  if (p.gface[d * 2 + side]) {
-    if (here) v = fixed_ghost(p, d, side, m, e);
-  } else {
-    v = p.ghost[(size_t)(d * 2 + side) * p.nang + m];
-  }
-  return true;
-}
-
 // A pointer into the constant address space: the angle records are read-only
 // for the whole step, and reads through such a pointer at a wave-uniform
 // address become scalar loads even after the step's global writes and
