@@ -259,7 +259,7 @@ int rt_step(rt_ctx *ctx, double dt, int nsteps, const rt_fields *f, rt_out *out,
  * context would allocate (angle tables, two moment fields, the interface
  * table, partial totals) is carved from a file-scope device array of
  * RT_STATIC_SCRATCH_BYTES per GPU instead, so a problem fits when it needs
- * about 282 bytes per cell plus 340 per direction (64^3 cells does not; 60^3
+ * about 282 bytes per cell plus 300 per direction (64^3 cells does not; 60^3
  * does); larger ones return RT_ETOOBIG before any device work.  Arguments,
  * layouts and results are those of the calls it stands for: I_a holds the
  * current intensities on entry; after the call the newest are in I_a when

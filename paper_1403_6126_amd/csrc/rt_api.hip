@@ -45,7 +45,6 @@ __global__ __launch_bounds__(kBlock) void k_faces(StepArgs p, double *faces, dou
         r[rec_n0 + d] = n[d];
         r[rec_h0 + d] = 1.0 - p.C * fabs(n[d]) * p.dt_dx[d];
         r[rec_wn0 + d] = w * n[d];
-        r[rec_s0 + d] = n[d] < 0.0 ? -r[rec_h0 + d] : r[rec_h0 + d];
       }
       r[rec_w] = w;
       r[rec_wnn + 0] = w * n[0] * n[0];
@@ -66,10 +65,10 @@ __global__ __launch_bounds__(kBlock) void k_faces(StepArgs p, double *faces, dou
       if (f == rec_flags) {
         unsigned long long bits = flags;
         arec[(size_t)c * kRec + f] = __longlong_as_double((long long)bits);
-        arecf[(size_t)c * kRec + f] = __uint_as_float(flags);
+        if (arecf) arecf[(size_t)c * kRec + f] = __uint_as_float(flags);
       } else {
         arec[(size_t)c * kRec + f] = r[f];
-        arecf[(size_t)c * kRec + f] = float(r[f]);
+        if (arecf) arecf[(size_t)c * kRec + f] = float(r[f]);
       }
     }
   }
@@ -328,12 +327,13 @@ int one_step(rt_ctx *c, double dt, const rt_fields *f, const void *dF, bool fuse
     c->pending.emplace_back(e0, e1);
   }
   if (last && o && o->totals) {
+    // chunk rows go into the interface table, which the last step has read
     const int nch = tot_chunks(a.nparts);
-    double *dst = nch > 1 ? c->chunks : o->totals;
+    double *dst = nch > 1 ? c->faces : o->totals;
     hipLaunchKernelGGL(k_totals, dim3((unsigned)nch), dim3(64 * kNtot), 0, s, c->partials,
                        a.nparts, dst);
     if (nch > 1)
-      hipLaunchKernelGGL(k_totals_join, dim3(1), dim3(64 * kNtot), 0, s, c->chunks, nch,
+      hipLaunchKernelGGL(k_totals_join, dim3(1), dim3(64 * kNtot), 0, s, c->faces, nch,
                          o->totals);
     if (!hip_ok(hipGetLastError())) return RT_EDEVICE;
   }
@@ -404,8 +404,6 @@ void ctx_fill_args(const rt_ctx *c, double dt_call, const rt_fields *f, StepArgs
   a.estimate_v = (c->p.flags & RT_ESTIMATE_V) ? 1 : 0;
   a.mu = c->d_mu;
   a.w = c->d_w;
-  a.muf = c->d_muf;
-  a.wf = c->d_wf;
   a.ghost = c->d_ghost;
   a.arec = c->d_arec;
   a.arecf = c->d_arecf;
@@ -511,7 +509,7 @@ int ctx_init_host(const rt_grid *g, const rt_angles *an, const rt_params *p, rt_
 namespace {
 // Scratch layout: offsets of the pieces in one block.
 struct Plan {
-  size_t mu, w, muf, wf, ghost, arec, arecf, mom0, mom1, faces, partials, chunks, status, total;
+  size_t mu, w, ghost, arec, arecf, mom0, mom1, faces, partials, status, total;
 };
 Plan plan_of(const rt_ctx *c) {
   Plan q;
@@ -524,16 +522,13 @@ Plan plan_of(const rt_ctx *c) {
   };
   q.mu = take(sizeof(double) * 3 * N);
   q.w = take(sizeof(double) * N);
-  q.muf = take(sizeof(float) * 3 * N);
-  q.wf = take(sizeof(float) * N);
   q.ghost = take(sizeof(double) * 6 * N);
   q.arec = take(sizeof(double) * kRec * (size_t)c->nrec);
-  q.arecf = take(sizeof(float) * kRec * (size_t)c->nrec);
+  q.arecf = take(c->p.precision == RT_FP32_MIXED ? sizeof(float) * kRec * (size_t)c->nrec : 0);
   q.mom0 = take(sizeof(double) * kNmomX * nc);
   q.mom1 = take(sizeof(double) * kNmomX * nc);
   q.faces = take(sizeof(double) * 9 * nc);
   q.partials = take(sizeof(double) * kNtot * c->nblocks);
-  q.chunks = take(sizeof(double) * kNtot * tot_chunks(c->nblocks));
   q.status = take(sizeof(int));
   q.total = o;
   return q;
@@ -548,39 +543,27 @@ int ctx_attach_scratch(rt_ctx *c, char *base, hipStream_t s, char *stage) {
   const size_t N = c->nang;
   c->d_mu = reinterpret_cast<double *>(base + q.mu);
   c->d_w = reinterpret_cast<double *>(base + q.w);
-  c->d_muf = reinterpret_cast<float *>(base + q.muf);
-  c->d_wf = reinterpret_cast<float *>(base + q.wf);
-  c->h_muf.assign(c->h_mu.begin(), c->h_mu.end());
-  c->h_wf.assign(c->h_w.begin(), c->h_w.end());
   c->d_ghost = reinterpret_cast<double *>(base + q.ghost);
   c->d_arec = reinterpret_cast<double *>(base + q.arec);
-  c->d_arecf = reinterpret_cast<float *>(base + q.arecf);
+  c->d_arecf = c->p.precision == RT_FP32_MIXED ? reinterpret_cast<float *>(base + q.arecf) : nullptr;
   c->mom[0] = reinterpret_cast<double *>(base + q.mom0);
   c->mom[1] = reinterpret_cast<double *>(base + q.mom1);
   c->faces = reinterpret_cast<double *>(base + q.faces);
   c->partials = reinterpret_cast<double *>(base + q.partials);
-  c->chunks = reinterpret_cast<double *>(base + q.chunks);
   c->status = reinterpret_cast<int *>(base + q.status);
   bool ok;
   if (stage) {  // the tables lie side by side: one copy
     std::memcpy(stage + q.mu, c->h_mu.data(), sizeof(double) * 3 * N);
     std::memcpy(stage + q.w, c->h_w.data(), sizeof(double) * N);
-    std::memcpy(stage + q.muf, c->h_muf.data(), sizeof(float) * 3 * N);
-    std::memcpy(stage + q.wf, c->h_wf.data(), sizeof(float) * N);
     std::memcpy(stage + q.ghost, c->h_ghost.data(), sizeof(double) * 6 * N);
     ok = hip_ok(hipMemcpyAsync(base, stage, q.arec, hipMemcpyHostToDevice, s));
   } else {
-    ok =
-      hip_ok(hipMemcpyAsync(c->d_mu, c->h_mu.data(), sizeof(double) * 3 * N,
-                            hipMemcpyHostToDevice, s)) &&
-      hip_ok(hipMemcpyAsync(c->d_w, c->h_w.data(), sizeof(double) * N, hipMemcpyHostToDevice,
-                            s)) &&
-      hip_ok(hipMemcpyAsync(c->d_muf, c->h_muf.data(), sizeof(float) * 3 * N,
-                            hipMemcpyHostToDevice, s)) &&
-      hip_ok(hipMemcpyAsync(c->d_wf, c->h_wf.data(), sizeof(float) * N, hipMemcpyHostToDevice,
-                            s)) &&
-      hip_ok(hipMemcpyAsync(c->d_ghost, c->h_ghost.data(), sizeof(double) * 6 * N,
-                            hipMemcpyHostToDevice, s));
+    ok = hip_ok(hipMemcpyAsync(c->d_mu, c->h_mu.data(), sizeof(double) * 3 * N,
+                               hipMemcpyHostToDevice, s)) &&
+         hip_ok(hipMemcpyAsync(c->d_w, c->h_w.data(), sizeof(double) * N, hipMemcpyHostToDevice,
+                               s)) &&
+         hip_ok(hipMemcpyAsync(c->d_ghost, c->h_ghost.data(), sizeof(double) * 6 * N,
+                               hipMemcpyHostToDevice, s));
   }
   if (!ok) return RT_EDEVICE;
   clear_stale_error();
@@ -673,8 +656,6 @@ __attribute__((constructor)) void static_ctx_init() {
     c->h_mu.reserve(3 * N);
     c->h_w.reserve(N);
     c->h_ghost.reserve(6 * N);
-    c->h_muf.reserve(3 * N);
-    c->h_wf.reserve(N);
     static_ctx[d] = c;
   }
 }

@@ -25,8 +25,7 @@ enum RecField : int {
   rec_wn0, rec_wn1, rec_wn2,    // w n_d
   rec_wnn,                      // 6 values: w n_x n_x, w n_y n_y, w n_z n_z, w n_x n_y, w n_x n_z, w n_y n_z
   rec_flags = rec_wnn + 6,      // integer bits in the slot: bit d n_d > 0, bit 3 + d n_d != 0
-  rec_s0, rec_s1, rec_s2,       // rec_h0.. with the sign of n_d
-  kRec = 20
+  kRec = 17
 };
 
 // Arguments of every step kernel (passed by value).
@@ -44,14 +43,12 @@ struct StepArgs {
   int maxit, estimate_v;
   const double *mu;      // [3][nang]
   const double *w;       // [nang]
-  const float *muf;      // FP32 copies of mu and w (FP32 arithmetic)
-  const float *wf;
   // per call, one record of kRec values per angle (padded with zero records
   // to the slots of the wave-group kernel): the direction, the Courant
   // factors 1 - C |mu_d| dt/dx_d of the slope terms, and the quadrature
   // weights of the moments (layout in rec_*)
   const double *arec;
-  const float *arecf;
+  const float *arecf;    // FP32 copies (contexts with FP32 intensities only)
   double wmom[10];       // sum w, w n_i, w n_i n_j (xx yy zz xy xz yz) of the angle set
   const double *ghost;   // [3][2][nang] fixed-face ghost intensities
   const double *gface[6];  // per face (axis*2 + side): [nang][ncell / n[axis]]

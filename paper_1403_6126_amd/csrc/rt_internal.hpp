@@ -109,7 +109,6 @@ struct rt_ctx {
   double wmom[10] = {};  // sum w, w n_i, w n_i n_j (xx yy zz xy xz yz)
   double cfl_sum = 0.0;  // max over angles of sum_d |mu_d| / dx_d
   std::vector<double> h_mu, h_w, h_ghost;
-  std::vector<float> h_muf, h_wf;       // FP32 copies of the angle table
   // device memory: one block when carved from a caller's arena, else
   // separate hipMalloc allocations owned by the context
   bool owns_device = true;
@@ -117,19 +116,18 @@ struct rt_ctx {
   // position-dependent ghost tables of fixed faces (axis*2 + side), each its
   // own allocation owned by the context
   double *d_gface[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  float *d_muf = nullptr, *d_wf = nullptr;
   int nrec = 0;                         // angle records (nang, padded to the kernel's slots)
   double *d_arec = nullptr;             // [nrec][kRec] per-call angle records
-  float *d_arecf = nullptr;
+  float *d_arecf = nullptr;             // with FP32 intensities only
   void *I[2] = {nullptr, nullptr};
   int cur = 0;
   double *mom[2] = {nullptr, nullptr};  // [13][ncell]: E, F, P, 3vJ
   int mom_cur = 0;
-  double *faces = nullptr;              // [3][3][ncell] interface table of the call
+  double *faces = nullptr;              // [3][3][ncell] interface table of the call; after its
+                                        // last step the first stage of the totals
   rtk::KShape shape;
   bool mom_valid = false;
   double *partials = nullptr;           // [kNtot][nblocks], kept over the steps of a call
-  double *chunks = nullptr;             // [kNtot][chunks of rows], first stage of the totals
   int *status = nullptr;
   long long nblocks = 0;
   bool profile = false;

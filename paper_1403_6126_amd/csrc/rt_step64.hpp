@@ -298,22 +298,24 @@ __device__ __forceinline__ void ghost_reads(const StepArgs &p, const unsigned (&
 // and at the upwind far cell (-1 for mu > 0, +2 for mu < 0): G relative to the
 // lower cell and Gp relative to the upper one.
 __device__ __forceinline__ void face_value(const Face64 &f, double n0, double n1, double n2,
-                                           double hs, bool pos, double I0, double I1, double If,
+                                           double h2, bool pos, double I0, double I1, double If,
                                            double invC, double &G, double &Gp) {
   const double V = n0 * f.w0[0] + n1 * f.w0[1] + n2 * f.w0[2];
   const double Vf = n0 * f.wf[0] + n1 * f.wf[1] + n2 * f.wf[2];
   const double cab = f.ca + f.cb;
-  double Vx, dx, k, kp;
+  double Vx, dx, k, kp, hs;
   if (pos) {
     Vx = n0 * f.wm[0] + n1 * f.wm[1] + n2 * f.wm[2];
     dx = I0 - If;
     k = f.cb;
     kp = cab;
+    hs = h2;
   } else {
     Vx = n0 * f.wp[0] + n1 * f.wp[1] + n2 * f.wp[2];
     dx = If - I1;
     k = cab;
     kp = f.cb;
+    hs = -h2;
   }
   const double D = fma_(-V, invC, I1 - I0), Dx = fma_(-Vx, invC, dx);
   const double q = vl_half(Dx, D), qv = vl_half(Vf, V);
@@ -395,9 +397,9 @@ struct Transport64 {
     double n0, n1, n2, mud, h;
     unsigned fl;
   };
-  __device__ static __forceinline__ Rec load_rec(const Set &s, int k, int d, int h) {
+  __device__ static __forceinline__ Rec load_rec(const Set &s, int k, int d) {
     const cptr<double> R = s.rec(k);
-    return Rec{R[rec_n0], R[rec_n1], R[rec_n2], R[rec_n0 + d], R[h + d], s.flags(k)};
+    return Rec{R[rec_n0], R[rec_n1], R[rec_n2], R[rec_n0 + d], R[rec_h0 + d], s.flags(k)};
   }
   __device__ __forceinline__ Set open() const {
     const int m = m0 + opaque_zero();
@@ -424,7 +426,7 @@ struct Transport64 {
 #pragma unroll
     for (int j = 0; j < PF; ++j)
       if (j < NS) reads(j, rq[j]);
-    Rec next = load_rec(set, 0, d, rec_s0);
+    Rec next = load_rec(set, 0, d);
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
       __builtin_amdgcn_sched_barrier(0);  // keeps the reads ahead where they are
@@ -433,7 +435,7 @@ struct Transport64 {
       for (int t = 0; t < 3; ++t) r[t] = rq[k % PF][t];
       if (k + PF < NS) reads(k + PF, rq[k % PF]);
       const Rec R = next;
-      if (k + 1 < NS) next = load_rec(set, k + 1, d, rec_s0);
+      if (k + 1 < NS) next = load_rec(set, k + 1, d);
       if (!((R.fl >> (3 + d)) & 1u)) continue;  // mu_d = 0, padding slots
       const bool pos = (R.fl >> d) & 1u;
       const double mud = R.mud;
@@ -461,7 +463,7 @@ struct Transport64 {
 #pragma unroll
     for (int j = 0; j < PF; ++j)
       if (j < NS) reads(j, rq[j]);
-    Rec next = load_rec(set, 0, d, rec_h0);
+    Rec next = load_rec(set, 0, d);
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
       __builtin_amdgcn_sched_barrier(0);  // keeps the reads ahead where they are
@@ -470,7 +472,7 @@ struct Transport64 {
       for (int t = 0; t < 4; ++t) r[t] = rq[k % PF][t];
       if (k + PF < NS) reads(k + PF, rq[k % PF]);
       const Rec R = next;
-      if (k + 1 < NS) next = load_rec(set, k + 1, d, rec_h0);
+      if (k + 1 < NS) next = load_rec(set, k + 1, d);
       if (!((R.fl >> (3 + d)) & 1u)) continue;
       const bool pos = (R.fl >> d) & 1u;
       const double n0 = R.n0, n1 = R.n1, n2 = R.n2, mud = R.mud, h2 = R.h;
@@ -526,7 +528,7 @@ __device__ __forceinline__ void start_faces(const StepArgs &p, int cfirst, int c
     double r0 = I[f.idx[1]], r1 = I[f.idx[2]], rf = I[pos ? f.idx[0] : f.idx[3]];
     if (!PER && __any(f.kinds != 0)) ghost_reads(p, f.idx, f.kinds, 0, m, pos, r0, r1, rf);
     double G, Gp;
-    face_value(f, mud, R[rec_n1], R[rec_n2], R[rec_s0], pos, r0, r1, rf, invC, G, Gp);
+    face_value(f, mud, R[rec_n1], R[rec_n2], R[rec_h0], pos, r0, r1, rf, invC, G, Gp);
     if (on) tab[k * kMaxStarts + j] = Gp;
   }
 }
