@@ -233,7 +233,7 @@ void pick_shape64(int nang, const rt_grid &g, long long ncell, KShape &k) {
   k.geo.slots = slots;
   const int nx = g.n[0];
   const int starts = nx % 64 == 0 ? 1 : 1 + (62 + nx) / nx;
-  k.geo.xs = nx >= 8 && slots >= 13 * ((slots * starts + 63) / 64);
+  k.geo.xs = nx >= 8 && slots >= kSharedSlots * ((slots * starts + 63) / 64);
 }
 
 long long cell_blocks(const rt_ctx *c) { return (c->ncell + kBlock - 1) / kBlock; }

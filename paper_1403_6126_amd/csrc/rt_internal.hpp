@@ -76,6 +76,9 @@ RT_DECLARE_STEP3(4)
 // larger than a block's waves hold run in chunks of kStagedSlots.
 #define RT_SLOTS64(X) X(1) X(2) X(3) X(4) X(5) X(6) X(8) X(10) X(12) X(15) X(20) X(24) X(30)
 constexpr int kStagedSlots = 10;
+// Angles per wave from which faces along x are shared between lanes
+// (pick_shape64): instances of fewer hold no code for it.
+constexpr int kSharedSlots = 13;
 enum Launch64 : int { kStep64 = 0, kSourceStep64 = 1, kTransportOnly64 = 2 };
 #define RT_DECLARE_STEP64(ns)                                                               \
   void launch_step64_##ns(const StepArgs &a, const KShape &k, Launch64 what, long long blocks, \

@@ -552,12 +552,15 @@ struct Tile64 {
 
   __device__ __forceinline__ Tile64(const StepArgs &p_, const Geo64 &q_, int blk, int G_,
                                     char *lds_, bool fused, bool transport)
-      : p(p_), q(q_), L(lds64(G_, NS, p_.ndim, q_.xs && fused, transport)), lds(lds_) {
+      : p(p_),
+        q(q_),
+        L(lds64(G_, NS, p_.ndim, NS >= kSharedSlots && q_.xs && fused, transport)),
+        lds(lds_) {
     lane = threadIdx.x & 63;
     // wave-uniform: the wave's angles and their records are scalars
     g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     G = G_;
-    xs = q.xs && fused;
+    xs = NS >= kSharedSlots && q.xs && fused;
     first = blk * 64;
     act = first + lane < p.ncell;
     c = act ? first + lane : p.ncell - 1;
@@ -650,6 +653,7 @@ struct Tile64 {
 template <int NS, bool PER, int MODE, bool SO, bool STAGED>
 struct Step64 {
   using Tile = Tile64<NS, PER>;
+  static_assert(!STAGED || NS < kSharedSlots, "the table of low x faces holds one chunk");
 
   // The transport increment alone.
   __device__ static __forceinline__ void transport(const StepArgs &p, const Geo64 &q, int blk,
@@ -712,11 +716,8 @@ struct Step64 {
 #pragma unroll
       for (int k = 0; k < NS; ++k) pk[k] = 0.0;
       if (ch == 0) t.build(MODE == kFused64, true);
-      if (MODE == kFused64 && t.xs) {
-        if (STAGED && ch > 0) __syncthreads();
-        t.starts(m0);
-      }
-      if (ch == 0 || t.xs) __syncthreads();
+      if (MODE == kFused64 && t.xs) t.starts(m0);
+      if (ch == 0) __syncthreads();
       // -------------------------------------------- phase A: transport
       if constexpr (MODE == kFused64) {
         t.transport(m0, pk);
