@@ -1120,11 +1120,17 @@ __global__ __launch_bounds__(64 * max_waves64(NS), NS <= 10 ? 4 : 3) void k_step
 }
 
 // The transport increment alone (rt_transport): the same faces, written to
-// dF_out; the angle chunks of a tile are separate blocks (blockIdx.y).
+// dF_out; the angle chunks of a tile are separate blocks (blockIdx.y).  The step's
+// arguments, the first of the kernel, are read where the launch put them: from the
+// parameter itself, whose tables the ghosts index by axis, the compiler made a copy
+// in scratch memory in the non-periodic instances of 20 and more angles (900 B and
+// 120 to 280 registers spilled a lane; 96 x 96 x 48 S8 between fixed, vacuum and copy
+// faces, transport and source: 1.76 ms so, 0.79 as it is).
 template <int NS, bool PER>
-__global__ __launch_bounds__(64 * max_waves64(NS), NS <= 10 ? 4 : 3) void k_transport64(StepArgs p,
+__global__ __launch_bounds__(64 * max_waves64(NS), NS <= 10 ? 4 : 3) void k_transport64(StepArgs,
                                                                                        Geo64 q) {
   extern __shared__ double lds_[];
+  const StepArgs &p = *(const StepArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   const int blk = slab_block((int)blockIdx.x, (int)gridDim.x, p.n, 4);
   Step64<NS, PER, kFused64, false, false>::transport(p, q, blk, (int)blockIdx.y,
                                                             blockDim.x >> 6,
