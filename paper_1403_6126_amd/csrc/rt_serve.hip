@@ -123,22 +123,83 @@ struct Batch {
   int slot = -1;
 };
 
-constexpr int kStageSlots = 8;
 constexpr int kMaxBatch = 512;
-// Streams of the packed launches, taken in turn: a packed solve occupies one CU
-// for milliseconds (11 us a tile of 80 angles and step), and launches of one stream run one
-// after the other.
+// Streams that may take a packed launch, each with at most one in flight: two of
+// their own and, while no large request runs, the stream of those.  A packed solve occupies one
+// CU for up to milliseconds (11 us a tile of 80 angles and step), so launches go
+// side by side, and what becomes ready while all streams are busy gathers into the
+// next launch: with launches queued behind each other a crowd of small requests
+// goes out in launches of one or two (400 slabs of 256 cells and 16 directions, 50
+// steps: 70 ms with one launch a stream, 83 with two).  The device has four
+// queues; the large requests need one that no packed stream shares (200 requests at
+// load 0.8: median latency of the large ones 1.04 s on a shared one, 0.78 on their
+// own), and two streams for packed launches are too few (twelve requests of up to
+// 66434 cells: 15.9 ms with two, 13.0 to 14.5 with three).
 constexpr int kPackStreams = 3;
 // Pinned staging of the uploads: a request whose tables and fields fit a slot goes
 // up in two asynchronous copies instead of ten from pageable memory (0.55 ms of
 // the IO thread each, in which no other request is admitted).
-constexpr int kUpSlots = 8;
-constexpr size_t kUpBytes = 1 << 20;
+// The staging is a ring of bytes, so that many small requests can be on their way:
+// waiting for an upload costs the thread more than the upload (300 slabs of 64 cells
+// and 8 directions, 50 steps: 43 ms; 66 with eight slots of 1 MiB).
+constexpr size_t kUpBytes = 1 << 20;       // largest request staged
+constexpr size_t kUpRing = 8 * kUpBytes;
+constexpr int kUpMax = 128;                // uploads on their way
 
-struct UpSlot {
-  char *mem = nullptr;
-  hipEvent_t done = nullptr;
-  bool used = false;
+class UpRing {
+ public:
+  bool init() {
+    if (hipHostMalloc((void **)&mem_, kUpRing, hipHostMallocDefault) != hipSuccess) {
+      mem_ = nullptr;
+      return false;
+    }
+    for (auto &e : done_)
+      if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        e = nullptr;
+        return false;
+      }
+    return true;
+  }
+  void destroy() {
+    if (mem_) hipHostFree(mem_);
+    for (auto e : done_)
+      if (e) hipEventDestroy(e);
+  }
+  // n bytes (at most kUpBytes) that no upload on its way reads; null if a wait fails.
+  char *take(size_t n) {
+    if (head_ + n > kUpRing) head_ = 0;
+    const size_t a = head_, b = head_ + n;
+    // oldest first: an upload is done when its event is, and so are those before it
+    while (count_ && (count_ == kUpMax || overlaps(a, b))) {
+      if (hipEventSynchronize(done_[first_]) != hipSuccess) return nullptr;
+      first_ = (first_ + 1) % kUpMax;
+      --count_;
+    }
+    const int k = (first_ + count_) % kUpMax;
+    from_[k] = a;
+    to_[k] = b;
+    ++count_;
+    head_ = b;
+    return mem_ + a;
+  }
+  // After the copies of the last take() are queued (also of failed ones: what was
+  // queued before may still be read).
+  bool queued(hipStream_t s) {
+    return hipEventRecord(done_[(first_ + count_ - 1) % kUpMax], s) == hipSuccess;
+  }
+
+ private:
+  bool overlaps(size_t a, size_t b) const {
+    for (int i = 0; i < count_; ++i) {
+      const int k = (first_ + i) % kUpMax;
+      if (from_[k] < b && a < to_[k]) return true;
+    }
+    return false;
+  }
+  char *mem_ = nullptr;
+  hipEvent_t done_[kUpMax] = {};
+  size_t from_[kUpMax] = {}, to_[kUpMax] = {}, head_ = 0;
+  int first_ = 0, count_ = 0;
 };
 
 }  // namespace
@@ -148,13 +209,11 @@ struct rt_server {
   int device = 0;
   Arena arena;
   hipStream_t s_io = nullptr, s_small = nullptr, s_large = nullptr;
-  hipStream_t s_pack[kPackStreams] = {};
-  int next_pack = 0;
-  UpSlot up[kUpSlots];  // IO thread only
-  int next_up = 0;
-  PackedJob *h_stage = nullptr;  // pinned [kStageSlots][kMaxBatch]
+  hipStream_t s_pack[2] = {};
+  UpRing up;  // IO thread only
+  PackedJob *h_stage = nullptr;  // pinned [kPackStreams][kMaxBatch]
   PackedJob *d_stage = nullptr;
-  bool slot_busy[kStageSlots] = {};
+  bool pack_busy[kPackStreams] = {};
   std::chrono::steady_clock::time_point t0;
 
   std::mutex mu;                  // guards the queues and the request map
@@ -245,30 +304,25 @@ bool rt_server::admit_one(Request *q) {
   hipStream_t s = s_io;
   // the fields lie side by side from sigma_a on
   const size_t n_tab = a256(ctx_table_bytes(&c)), n_fld = (size_t)((char *)q->d_E - (char *)q->d_sa);
-  UpSlot *slot = n_tab + n_fld <= kUpBytes ? &up[next_up] : nullptr;
-  bool ok = true;
+  const bool staged = n_tab + n_fld <= kUpBytes;
+  char *slot = staged ? up.take(n_tab + n_fld) : nullptr;
+  bool ok = slot || !staged;
   auto put = [&](void *dst, const void *src, size_t bytes) {
     if (slot)
-      std::memcpy(slot->mem + n_tab + ((char *)dst - (char *)q->d_sa), src, bytes);
+      std::memcpy(slot + n_tab + ((char *)dst - (char *)q->d_sa), src, bytes);
     else
       ok = ok && hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
   };
-  if (slot) {
-    next_up = (next_up + 1) % kUpSlots;
-    if (slot->used) ok = hipEventSynchronize(slot->done) == hipSuccess;
-    slot->used = true;
-  }
-  ok = ok && ctx_attach_scratch(&c, scratch, s, slot ? slot->mem : nullptr) == RT_OK;
+  ok = ok && ctx_attach_scratch(&c, scratch, s, slot) == RT_OK;
   put(q->d_sa, r.sigma_a, sizeof(double) * nc);
   put(q->d_ss, r.sigma_s, sizeof(double) * nc);
   put(q->d_rho, r.rho, sizeof(double) * nc);
   put(q->d_T, r.T, sizeof(double) * nc);
   put(q->d_v, r.v, sizeof(double) * 3 * nc);
   if (slot) {
-    ok = ok && hipMemcpyAsync(q->d_sa, slot->mem + n_tab, n_fld, hipMemcpyHostToDevice, s) ==
+    ok = ok && hipMemcpyAsync(q->d_sa, slot + n_tab, n_fld, hipMemcpyHostToDevice, s) ==
                    hipSuccess;
-    // also after a failed copy: what was queued before it may still be read
-    if (hipEventRecord(slot->done, s) != hipSuccess) ok = false;
+    if (!up.queued(s)) ok = false;
   }
   if (r.I0)
     ok = ok && hipMemcpyAsync(q->d_I[0], r.I0, sb * c.nang * nc, hipMemcpyHostToDevice, s) ==
@@ -415,10 +469,13 @@ void rt_server::sched_loop() {
     }
     bool progress = false;
     // packed launches: one per angle-group class and boundary class
+    hipStream_t const pack_stream[kPackStreams] = {s_pack[0], s_large, s_pack[1]};
+    bool taken[kPackStreams] = {};
+    for (const Request *q : running) taken[1] = taken[1] || q->large;
     while (!to_pack.empty()) {
       int slot = -1;
-      for (int i = 0; i < kStageSlots; ++i)
-        if (!slot_busy[i]) {
+      for (int i = 0; i < kPackStreams; ++i)
+        if (!pack_busy[i] && !taken[i]) {
           slot = i;
           break;
         }
@@ -437,8 +494,7 @@ void rt_server::sched_loop() {
           rest.push_back(q);
       }
       to_pack.swap(rest);
-      hipStream_t s_batch = s_pack[next_pack];
-      next_pack = (next_pack + 1) % kPackStreams;
+      hipStream_t s_batch = pack_stream[slot];
       PackedJob *hj = h_stage + (size_t)slot * kMaxBatch;
       PackedJob *dj = d_stage + (size_t)slot * kMaxBatch;
       int tiles = 1;  // of the largest solve
@@ -466,7 +522,7 @@ void rt_server::sched_loop() {
                hipSuccess;
       b.ev = new_event();
       ok = ok && b.ev && hipEventRecord(b.ev, s_batch) == hipSuccess;
-      slot_busy[slot] = true;
+      pack_busy[slot] = true;
       for (Request *q : b.reqs) {
         q->ev_done = b.ev;
         if (!ok) q->status = RT_EDEVICE;
@@ -524,7 +580,7 @@ void rt_server::sched_loop() {
     for (size_t i = 0; i < batches.size();) {
       if (event_done(batches[i].ev)) {
         for (Request *q : batches[i].reqs) finished.push_back(q);
-        slot_busy[batches[i].slot] = false;
+        pack_busy[batches[i].slot] = false;
         // the IO thread waits on the event before it is destroyed below
         hipEventSynchronize(batches[i].ev);
         for (Request *q : batches[i].reqs) q->ev_done = nullptr;
@@ -555,14 +611,9 @@ namespace {
 
 // The server's streams and upload staging.
 void free_streams(rt_server *s) {
-  for (hipStream_t st : {s->s_io, s->s_small, s->s_large})
+  for (hipStream_t st : {s->s_io, s->s_small, s->s_large, s->s_pack[0], s->s_pack[1]})
     if (st) hipStreamDestroy(st);
-  for (hipStream_t st : s->s_pack)
-    if (st) hipStreamDestroy(st);
-  for (auto &u : s->up) {
-    if (u.mem) hipHostFree(u.mem);
-    if (u.done) hipEventDestroy(u.done);
-  }
+  s->up.destroy();
 }
 
 }  // namespace
@@ -581,16 +632,10 @@ int rt_serve_create(const rt_serve_config *cfg, rt_server **out) {
   hipGetDevice(&s->device);
   s->t0 = std::chrono::steady_clock::now();
   bool ok = s->arena.init(cfg->pool_bytes);
-  ok = ok && hipStreamCreateWithFlags(&s->s_io, hipStreamNonBlocking) == hipSuccess;
-  for (auto &u : s->up) {
-    ok = ok && hipHostMalloc((void **)&u.mem, kUpBytes, hipHostMallocDefault) == hipSuccess;
-    ok = ok && (u.done = new_event()) != nullptr;
-  }
-  ok = ok && hipStreamCreateWithFlags(&s->s_small, hipStreamNonBlocking) == hipSuccess;
-  for (auto &st : s->s_pack)
-    ok = ok && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess;
-  ok = ok && hipStreamCreateWithFlags(&s->s_large, hipStreamNonBlocking) == hipSuccess;
-  const size_t stage = sizeof(PackedJob) * kStageSlots * kMaxBatch;
+  for (hipStream_t *st : {&s->s_io, &s->s_small, &s->s_large, &s->s_pack[0], &s->s_pack[1]})
+    ok = ok && hipStreamCreateWithFlags(st, hipStreamNonBlocking) == hipSuccess;
+  ok = ok && s->up.init();
+  const size_t stage = sizeof(PackedJob) * kPackStreams * kMaxBatch;
   ok = ok && hipHostMalloc((void **)&s->h_stage, stage, hipHostMallocDefault) == hipSuccess;
   ok = ok && hipMalloc((void **)&s->d_stage, stage) == hipSuccess;
   if (!ok) {
