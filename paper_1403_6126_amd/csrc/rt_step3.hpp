@@ -865,8 +865,11 @@ k_step3(StepArgs p) {
   step3_tile<S, A, KA, NG, PER, FUSED, SO>(p, blk, g, blockDim.x >> 6, lds_);
 }
 
-// Waves of a packed workgroup: with one or two angle groups per wave sixteen (128
-// registers), else eight.
+// Waves of a packed workgroup: with one or two angle groups per wave up to sixteen,
+// which holds them to 128 registers and spills (50 to 660), else eight.  Launches whose
+// teams fit eight waves (a solve of one or two tiles) take the instance bounded
+// to eight, which does not (60 cells, 80 directions, 50 steps, served alone: 6.3 ms
+// with sixteen, 5.8 with eight).
 constexpr int packed_waves(int NG) { return NG <= 2 ? 16 : 8; }
 constexpr size_t kLdsPerCu = 160 * 1024;
 
@@ -878,8 +881,8 @@ constexpr size_t kLdsPerCu = 160 * 1024;
 // (17 us a tile of 80 angles; four teams take four tiles in about 45).  Between
 // steps the workgroup fences its global writes (I, moments, T, partials) before
 // any wave reads them.
-template <typename S, typename A, int KA, int NG, bool PER>
-__global__ __launch_bounds__(64 * packed_waves(NG)) void k_step3_packed(
+template <typename S, typename A, int KA, int NG, bool PER, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_step3_packed(
     const PackedJob *__restrict__ jobs, int G, int team_lds) {
   extern __shared__ double lds_[];
   const PackedJob &J = jobs[blockIdx.x];

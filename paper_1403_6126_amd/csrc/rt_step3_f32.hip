@@ -23,6 +23,24 @@ void step3_launch(const StepArgs &a, const KShape &k, long long blocks, hipStrea
                        s, a);
 }
 
+struct PackedLaunch {
+  dim3 grid, block;
+  size_t lds;
+  const PackedJob *jobs;
+  int waves, team_lds;
+  bool periodic;
+};
+
+template <int WAVES>
+void packed_launch(const PackedLaunch &l, hipStream_t s) {
+  if (l.periodic)
+    hipLaunchKernelGGL((k_step3_packed<float, float, kAnglesPerWave, RT_NG, true, WAVES>), l.grid,
+                       l.block, l.lds, s, l.jobs, l.waves, l.team_lds);
+  else
+    hipLaunchKernelGGL((k_step3_packed<float, float, kAnglesPerWave, RT_NG, false, WAVES>), l.grid,
+                       l.block, l.lds, s, l.jobs, l.waves, l.team_lds);
+}
+
 }  // namespace
 
 void RT_CAT(launch_step3_f32_, RT_NG)(const StepArgs &a, const KShape &k, bool fused,
@@ -45,14 +63,12 @@ void RT_CAT(launch_packed_f32_, RT_NG)(const PackedJob *jobs, int njobs, int wav
   if (teams > fit) teams = fit;
   if (teams > tiles) teams = tiles;
   if (teams < 1) teams = 1;
-  const dim3 g((unsigned)njobs), b(64 * waves * teams);
-  const int team_lds = (int)(lds / sizeof(double));
-  if (periodic)
-    hipLaunchKernelGGL((k_step3_packed<float, float, kAnglesPerWave, RT_NG, true>), g, b,
-                       lds * teams, s, jobs, waves, team_lds);
+  const PackedLaunch l{dim3((unsigned)njobs), dim3(64 * waves * teams), lds * teams, jobs, waves,
+                       (int)(lds / sizeof(double)), periodic};
+  if (waves * teams <= kMaxWaves)
+    packed_launch<kMaxWaves>(l, s);
   else
-    hipLaunchKernelGGL((k_step3_packed<float, float, kAnglesPerWave, RT_NG, false>), g, b,
-                       lds * teams, s, jobs, waves, team_lds);
+    packed_launch<packed_waves(RT_NG)>(l, s);
 }
 
 }  // namespace rtk
