@@ -20,9 +20,9 @@
  *   - a scheduler thread runs admitted requests concurrently: FP32-mixed
  *     requests of at most packed_cells cells are packed into persistent
  *     launches in which one workgroup advances a whole solve (up to three
- *     launches at a time); every other
- *     request advances by chunks of about chunk_work cell-angle updates,
- *     at most two chunks in flight per request, on one of two streams: the
+ *     launches at a time); every other request advances by chunks of about
+ *     chunk_work cell-angle updates, at most two chunks in flight per
+ *     request, on one of two streams: the
  *     requests of at least large_work updates per step run one at a time in
  *     submission order on the first, the others round-robin on the second,
  *     so that requests arriving while others run start at once and their

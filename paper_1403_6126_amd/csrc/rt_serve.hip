@@ -125,23 +125,23 @@ struct Batch {
 
 constexpr int kMaxBatch = 512;
 // Streams that may take a packed launch, each with at most one in flight: two of
-// their own and, while no large request runs, the stream of those.  A packed solve occupies one
-// CU for up to milliseconds (11 us a tile of 80 angles and step), so launches go
-// side by side, and what becomes ready while all streams are busy gathers into the
-// next launch: with launches queued behind each other a crowd of small requests
-// goes out in launches of one or two (400 slabs of 256 cells and 16 directions, 50
-// steps: 70 ms with one launch a stream, 83 with two).  The device has four
-// queues; the large requests need one that no packed stream shares (200 requests at
-// load 0.8: median latency of the large ones 1.04 s on a shared one, 0.78 on their
-// own), and two streams for packed launches are too few (twelve requests of up to
-// 66434 cells: 15.9 ms with two, 13.0 to 14.5 with three).
+// their own and, while no large request runs, the stream of those.  A packed solve
+// occupies one CU for up to milliseconds (11 us a tile of 80 angles and step), so
+// launches go side by side, and what becomes ready while all streams are busy
+// gathers into the next launch: with launches queued behind each other a crowd of
+// small requests goes out in launches of one or two (400 slabs of 256 cells and 16
+// directions, 50 steps: 70 ms with one launch a stream, 83 with two).  The device
+// has four queues; the large requests need one that no packed stream shares (200
+// requests at load 0.8: median latency of the large ones 1.04 s on a shared one,
+// 0.78 on their own), and two streams for packed launches are too few (twelve
+// requests of up to 66434 cells: 15.9 ms with two, 13.0 to 14.5 with three).
 constexpr int kPackStreams = 3;
-// Pinned staging of the uploads: a request whose tables and fields fit a slot goes
+// Pinned staging of the uploads: a request of up to kUpBytes of tables and fields goes
 // up in two asynchronous copies instead of ten from pageable memory (0.55 ms of
-// the IO thread each, in which no other request is admitted).
-// The staging is a ring of bytes, so that many small requests can be on their way:
-// waiting for an upload costs the thread more than the upload (300 slabs of 64 cells
-// and 8 directions, 50 steps: 43 ms; 66 with eight slots of 1 MiB).
+// the IO thread, in which no other request is admitted).  The staging is a ring of
+// bytes, so that many small requests can be on their way: waiting for an upload
+// costs the thread more than the upload (300 slabs of 64 cells and 8 directions, 50
+// steps: 43 ms; 66 with eight slots of 1 MiB).
 constexpr size_t kUpBytes = 1 << 20;       // largest request staged
 constexpr size_t kUpRing = 8 * kUpBytes;
 constexpr int kUpMax = 128;                // uploads on their way

@@ -17,12 +17,12 @@
 //
 // What bounds it: instruction issue and the latency of the waves, not HBM
 // (128^3 S8: 3.2 GB of algorithmic bytes, 0.7 ms at the rate of a large copy).
-// Each of an axis's two faces costs two limiters with a reciprocal each and
-// the IV differences, about 40 instructions, so faces are shared
-// along x a lane computes its high face and takes the low one from the lane below
-// (a DPP wave shift); the low faces of the few lanes that have no such neighbour
-// (lane 0 and the first cell of a row) are computed together, one lane per
-// (angle, cell), before phase A.  The other axes form both faces in each cell.
+// Each of an axis's two faces costs two limiters with a reciprocal each and the IV
+// differences, about 40 instructions.  Faces along x are therefore shared: a lane
+// computes its high face and takes the low one from the lane below (a DPP wave
+// shift); the low faces of the few lanes that have no such neighbour (lane 0 and
+// the first cell of a row) are computed together, one lane per (angle, cell),
+// before phase A.  The other axes form both faces in each cell.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
