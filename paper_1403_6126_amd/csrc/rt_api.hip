@@ -26,7 +26,7 @@ namespace rtk {
 //          down, 1/2 at u = 0 (centred);
 //   j = 2  the signed van Leer factor of the IV value, sign(u) (1 - nu_v),
 //          nu_v = |u| dt/dx (0 at u = 0).
-// arec[m*kRec + f] (FP64, and FP32 copies) are the per-angle records of the
+// arec[m*kRec + f] (and FP32 copies unless arecf is null) are the per-angle records of the
 // call: direction, 1 - C |mu_d| dt/dx_d, w, w n_d, w n_i n_j and the sign
 // bits of the direction (as integers in the slot's low word); records
 // nang .. nrec-1 (the padding slots of the wave-group kernel) are zero.
